@@ -66,9 +66,12 @@ Stage *g_free[KEEP];  // idle pairs
 size_t g_nfree = 0;
 int g_users = 0;
 
-hipError_t stage_take(Stage **out) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
+// a pair for a stream: its events belong to the stream's device, whichever
+// device is the calling thread's current one
+hipError_t stage_take(hipStream_t st, Stage **out) {
+  int dev = 0, was = 0;
+  hipError_t e = hipStreamGetDevice(st, &dev);
+  if (e == hipSuccess) e = hipGetDevice(&was);
   if (e != hipSuccess) return e;
   {
     std::lock_guard<std::mutex> lk(g_mu);
@@ -82,9 +85,14 @@ hipError_t stage_take(Stage **out) {
   Stage *s = new (std::nothrow) Stage();
   if (!s) return hipErrorOutOfMemory;
   s->dev = dev;
+  if (was != dev) e = hipSetDevice(dev);
   for (int q = 0; q < 2 && e == hipSuccess; ++q) {
     e = hipHostMalloc((void **)&s->buf[q], SLAB, hipHostMallocDefault);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&s->ev[q], hipEventDisableTiming);
+  }
+  if (was != dev) {
+    const hipError_t back = hipSetDevice(was);
+    if (e == hipSuccess) e = back;
   }
   if (e != hipSuccess) {
     stage_free(s);
@@ -127,7 +135,7 @@ hipError_t field_io(hipStream_t st, const dfk::Geo &G, bool fp32, void *dev, con
   const size_t count = (size_t)e[0] * e[1] * e[2];  // below 2^31: a level's entries are
   const size_t slab = SLAB / sizeof(double), nslab = (count + slab - 1) / slab;
   Stage *s = nullptr;
-  hipError_t rc = stage_take(&s);
+  hipError_t rc = stage_take(st, &s);
   if (rc != hipSuccess) return rc;
   auto launch = [&](size_t k) -> hipError_t {
     const unsigned a0 = (unsigned)(k * slab), n = (unsigned)std::min(slab, count - k * slab);
