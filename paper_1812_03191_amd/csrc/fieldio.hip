@@ -15,6 +15,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 
@@ -130,13 +131,49 @@ User::~User() {
   while (n) stage_free(drop[--n]);
 }
 
+namespace {
+
+// The copy without staging buffers, where none can be had: the field's padded
+// rows as they are to pageable memory, and the values between there and the
+// caller's; in the other direction the rows' other entries go back unchanged.
+template <typename T>
+hipError_t field_io_pageable(hipStream_t st, const dfk::Geo &G, T *dev, const int e[3], double back, double *out,
+                             const double *in) {
+  const size_t n = (size_t)e[0] + (size_t)(e[1] - 1) * G.sy + (size_t)(e[2] - 1) * G.sz;
+  const std::unique_ptr<T[]> raw(new (std::nothrow) T[n]);
+  if (!raw) return hipErrorOutOfMemory;
+  dev += G.off;
+  hipError_t rc = hipMemcpyAsync(raw.get(), dev, n * sizeof(T), hipMemcpyDeviceToHost, st);
+  if (rc == hipSuccess) rc = hipStreamSynchronize(st);
+  if (rc != hipSuccess) return rc;
+  size_t a = 0;
+  for (int k = 0; k < e[2]; ++k)
+    for (int j = 0; j < e[1]; ++j) {
+      T *row = raw.get() + (size_t)j * G.sy + (size_t)k * G.sz;
+      for (int i = 0; i < e[0]; ++i, ++a) {
+        if (out) out[a] = back + (double)row[i];
+        else row[i] = (T)(in[a] - back);
+      }
+    }
+  if (out) return hipSuccess;
+  rc = hipMemcpyAsync(dev, raw.get(), n * sizeof(T), hipMemcpyHostToDevice, st);
+  const hipError_t end = hipStreamSynchronize(st);
+  return rc != hipSuccess ? rc : end;
+}
+
+}  // namespace
+
 hipError_t field_io(hipStream_t st, const dfk::Geo &G, bool fp32, void *dev, const int e[3], double back, double *out,
                     const double *in) {
   const size_t count = (size_t)e[0] * e[1] * e[2];  // below 2^31: a level's entries are
   const size_t slab = SLAB / sizeof(double), nslab = (count + slab - 1) / slab;
   Stage *s = nullptr;
   hipError_t rc = stage_take(st, &s);
-  if (rc != hipSuccess) return rc;
+  if (rc != hipSuccess) {
+    (void)hipGetLastError();  // (the next launch is not to report it)
+    if (fp32) return field_io_pageable<float>(st, G, (float *)dev, e, back, out, in);
+    return field_io_pageable<double>(st, G, (double *)dev, e, back, out, in);
+  }
   auto launch = [&](size_t k) -> hipError_t {
     const unsigned a0 = (unsigned)(k * slab), n = (unsigned)std::min(slab, count - k * slab);
     const dim3 gr((n + 255) / 256), bl(256);

@@ -178,6 +178,14 @@ int main(int argc, char **argv) {
     check(roundtrip(st0, 20, 10, 6, false) && roundtrip(st1, 20, 10, 6, false), "the same from the other device");
     check(roundtrip(nullptr, 20, 10, 6, false), "the null stream");
     check(g_pinned == 4, "one idle pair of buffers per device");
+  } else if (what == "no pinned memory") {
+    dfio::User run;
+    g_no_pinned = true;
+    check(roundtrip(st0, 2, 2, 2, false) && roundtrip(st0, 2, 2, 2, true), "fields of eight values");
+    check(roundtrip(st0, 130, 97, 61, false) && roundtrip(st0, 130, 97, 61, true), "fields of more than a slab");
+    check(hipGetLastError() == hipSuccess, "no error left for the next launch");
+    g_no_pinned = false;
+    check(roundtrip(st0, 130, 97, 61, false) && g_pinned == 2, "staging buffers again once they can be had");
   } else {
     check(false, "unknown check");
   }

@@ -22,7 +22,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["device"])
+@pytest.mark.parametrize("what", ["device", "no pinned memory"])
 def test_field_copies(program, what):
     res = subprocess.run([program, what], capture_output=True, text=True, timeout=60)
     print(res.stdout)
