@@ -26,9 +26,13 @@
  * Memory and streams: the caller owns a device arena (for instance a uint8
  * tensor) and a HIP stream; the library carves every buffer out of the arena
  * and launches every kernel on that stream.  Both must outlive the run.  The
- * library owns the opaque handles and their host metadata.  Host buffers
- * passed in or out belong to the caller.  A handle is not thread-safe: use it
- * from one host thread at a time.
+ * library owns the opaque handles and their host metadata, and pinned host
+ * memory through which fields are copied (df_get_field, df_set_field,
+ * df_engine_get_field): two buffers of 4 MiB, made by the first such call and
+ * kept while any run or engine exists (one pair per thread that copies at the
+ * same time and per device, at most four kept); where none can be had the copy
+ * goes through pageable memory.  Host buffers passed in or out belong to the
+ * caller.  A handle is not thread-safe: use it from one host thread at a time.
  *
  * Errors: every function returns DF_OK (0) or a negative DF_E* code;
  * df_strerror() names a code and df_last_error() returns the text of the last

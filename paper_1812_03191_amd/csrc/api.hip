@@ -1144,6 +1144,7 @@ struct Pending {
 }  // namespace
 
 struct df_engine {
+  dfio::User io;  // the field copies' staging outlives the jobs that used it
   char *base = nullptr;
   size_t bytes = 0;
   hipStream_t main = nullptr, admin = nullptr;

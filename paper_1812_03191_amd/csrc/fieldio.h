@@ -13,7 +13,8 @@ namespace dfio {
 hipError_t field_io(hipStream_t st, const dfk::Geo &G, bool fp32, void *dev, const int e[3], double back,
                     double *out, const double *in);
 
-// A run that may use the staging buffers: they are freed with the last one.
+// A run or engine that may use the staging buffers: they are freed with the
+// last one.
 struct User {
   User();
   ~User();
