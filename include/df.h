@@ -64,7 +64,9 @@ typedef struct df_run df_run;
 /* Mesh description (Sect. 3.4).
  *  nx, ny, nz : active cells of level 0 (and of every level unless nx1 is
  *               set), each even (the perturber is a vertex), each a multiple
- *               of 4 and >= 16 when nlevels > 1;
+ *               of 4 and >= 16 when nlevels > 1, at most 4096; no field of a
+ *               level, rows padded to 16 entries and finer levels with their
+ *               ghosts, may hold 2^31 entries or exceed 4 GiB;
  *  nlevels    : 1..12;
  *  dx0        : cell size of level 0 (> 0);
  *  gamma      : adiabatic index (> 1); cfl: Courant factor in (0, 1];

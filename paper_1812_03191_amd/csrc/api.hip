@@ -670,9 +670,10 @@ int df_init_mesh(const df_mesh_desc *d, df_run **out) {
       G.mg[k] = 1 << 20;  // no margin: the whole stored box
     }
     R->vol[l] = (size_t)G.sz * G.s[2];
-    if (R->vol[l] >= ((size_t)1 << 31)) {
+    // the kernels' lanes hold 32-bit entry indices and byte offsets
+    if (R->vol[l] >= ((size_t)1 << 31) || R->vol[l] * R->esz > ((size_t)1 << 32)) {
       delete R;
-      return fail(DF_EINVAL, "a level holds 2^31 entries or more per field");
+      return fail(DF_EINVAL, "a field of one level would hold 2^31 entries or exceed 4 GiB");
     }
     // frontier accumulators of a fine level: [dir][side][quantity][face]
     R->acc_n[l] = (l > 0) ? (size_t)3 * 2 * NQ * dfk::level_faces(G) : 0;

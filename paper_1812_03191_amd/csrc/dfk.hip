@@ -124,8 +124,8 @@ __device__ __forceinline__ bool thread_cell_flat(const Box &b, int &i, int &j, i
   return f < ex * ey;
 }
 
-// Element indices are 32-bit (a field holds fewer than 2^31 entries, checked
-// when a mesh is created): with a uniform 64-bit base in scalar registers the
+// Element indices are 32-bit (a field holds fewer than 2^31 entries and at most
+// 4 GiB, checked when a mesh is created): with a uniform 64-bit base in scalar registers the
 // loads and stores then take a 32-bit per-lane offset, with no 64-bit address
 // arithmetic per lane.
 using idx_t = int;
@@ -139,7 +139,7 @@ __device__ __forceinline__ idx_t dstride(const Geo &G, int d) {
 }
 
 // Load and store at a non-negative element index whose byte offset fits 32
-// bits (every field is smaller than 4 GiB): the address is a uniform base plus
+// bits (no field exceeds 4 GiB): the address is a uniform base plus
 // an unsigned 32-bit lane offset, which the hardware adds itself.
 template <typename T>
 __device__ __forceinline__ T gld(const T *p, idx_t i) {
@@ -186,7 +186,8 @@ __device__ __forceinline__ void gstv(T *p, idx_t i, V v) {
 // Loads and stores through a buffer descriptor, for accesses that a few lanes of
 // a wave make: a lane whose byte offset lies past the buffer's end (BUF_NONE and
 // a little more) reads zero and stores nothing, so the others' accesses need no
-// branch.  Buffers are smaller than 3 GiB.
+// branch.  Buffers are smaller than 3 GiB (the frontier's: 16 faces of at most
+// 4096^2 values, 2 GiB).
 constexpr unsigned BUF_NONE = 0xC0000000u;
 using Buf = __amdgpu_buffer_rsrc_t;
 __device__ __forceinline__ Buf make_buf(const void *p, unsigned bytes) {
