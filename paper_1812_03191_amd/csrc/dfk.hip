@@ -1143,6 +1143,16 @@ __device__ __forceinline__ void row_load(const T *p, idx_t c, T (&out)[R]) {
   for (int r = 0; r < R; ++r) out[r] = w[r];
 }
 
+// the same from any index
+template <typename T, int R>
+__device__ __forceinline__ void row_load_any(const T *p, idx_t c, T (&out)[R]) {
+  typedef T vec __attribute__((ext_vector_type(R), aligned(sizeof(T))));
+  const vec w = *reinterpret_cast<const vec *>(reinterpret_cast<const char *>(p) +
+                                                (unsigned)c * (unsigned)sizeof(T));
+#pragma unroll
+  for (int r = 0; r < R; ++r) out[r] = w[r];
+}
+
 template <typename T, int R>
 __device__ __forceinline__ void row_store(T *p, idx_t c, const T (&v)[R]) {
   typedef T vec __attribute__((ext_vector_type(R)));
@@ -1954,8 +1964,11 @@ struct XyGrid {
   }
   __device__ __forceinline__ idx_t at(int r) const { return lin(*G, L.xl, row(r), L.t); }
   // momenta tangential to x (their velocities): past the flow end x_max under
-  // bc 2 the last cell's value, read by the lane after it one entry early
-  __device__ __forceinline__ idx_t tangential() const { return XB == 2 && L.x0 == G->n[0] ? -1 : 0; }
+  // bc 2 the last cell's value, read by the lane after it one entry early (an
+  // odd index; what it then reads for the cell after that, the row's padding, is
+  // not used: it enters the first one's limited difference only, whose other
+  // factor, the difference of two equal values, is zero)
+  __device__ __forceinline__ idx_t tangential() const { return L.x0 == G->n[0] ? -1 : 0; }
 };
 
 // Frontier transfers of a walk (FR, bit 0: the level has a finer one whose
@@ -2089,7 +2102,9 @@ struct XyOwn {
         if (m == 1) row_load<T, W>(A.qi[1], c, in[u]);
         if (m >= 4) {
           const int d = (m - 2) >> 1;
-          row_load<T, W>(A.v[d], c + Q.tangential() + ((m & 1) ? dstride(*Q.G, d) : 0), in[u]);
+          const idx_t f = c + ((m & 1) ? dstride(*Q.G, d) : 0);
+          if constexpr (XB == 2) row_load_any<T, W>(A.v[d], f + Q.tangential(), in[u]);
+          else row_load<T, W>(A.v[d], f, in[u]);
         }
         if (FR & 1) fn[u] = X.fine_x(m, Q.row(r));
       }
