@@ -289,15 +289,20 @@ int df_debug_stage(df_run *run, int32_t stage, double dt);
  * pass after each step that forms both the force partials and the next step's
  * signal speeds, with the one-block kernel that logs the force and sets the
  * next time step; DF_K_DT is the time step before the first step of a df_step
- * call (with a signal pass if the state was changed by other calls);
+ * call (with a signal pass if the state was changed by other calls; under
+ * df_set_subcycling mode 1 before every step);
  * DF_K_PASSXY the fused x and y transport passes (df_set_transport_fusion),
  * DF_K_KICKCOMP the fused first kick and compression (df_set_kick_fusion),
  * DF_K_ZFINISH the z pass fused with the rebuild and kick
- * (df_set_finish_fusion). */
+ * (df_set_finish_fusion), DF_K_FRONT the sums of a finer level's frontier
+ * transfers over its sub-steps, before its parent's passes.  DF_K_ZERO is
+ * always 0: those transfers are stored, no longer added up in cleared memory.
+ * nkinds may be smaller than DF_K_NKINDS: the kinds from there on are left
+ * out. */
 enum {
   DF_K_KICK = 0, DF_K_COMPRESS, DF_K_DIFFUSE, DF_K_PASSX, DF_K_PASSY, DF_K_PASSZ, DF_K_REBUILD,
   DF_K_COMMUP, DF_K_COMMMEAN, DF_K_DT, DF_K_FORCE, DF_K_ZERO, DF_K_VISC, DF_K_PASSXY, DF_K_KICKCOMP,
-  DF_K_ZFINISH, DF_K_NKINDS
+  DF_K_ZFINISH, DF_K_FRONT, DF_K_NKINDS
 };
 int df_timing_enable(df_run *run, int32_t max_launches);
 int df_timing_read(df_run *run, double *ms, int32_t *count, int32_t nkinds);

@@ -187,7 +187,7 @@ def force_log(h, cap: int = 4096) -> np.ndarray:
 
 KERNEL_KINDS = ("kick", "compress", "diffuse_heat", "pass_x", "pass_y", "pass_z", "rebuild_kick",
                 "commup", "commmean", "dt", "force", "zero", "viscosity", "pass_xy", "kick_compress",
-                "pass_z_finish")
+                "pass_z_finish", "front")
 
 
 def timing_enable(h, max_launches: int) -> None:

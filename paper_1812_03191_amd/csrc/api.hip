@@ -184,7 +184,7 @@ void heat_table(const Geo &G, double sigma, double mult, std::vector<double> &w,
 // ---------------------------------------------------------------- timing
 // Kernel kinds timed by df_timing_read (the order of the DF_K_* list in df.h).
 enum { K_KICK = 0, K_COMPRESS, K_DIFFUSE, K_PASSX, K_PASSY, K_PASSZ, K_REBUILD, K_COMMUP, K_COMMMEAN,
-       K_DT, K_FORCE, K_ZERO, K_VISC, K_PASSXY, K_KICKCOMP, K_ZFINISH, K_NKINDS };
+       K_DT, K_FORCE, K_ZERO, K_VISC, K_PASSXY, K_KICKCOMP, K_ZFINISH, K_FRONT, K_NKINDS };
 static_assert(K_NKINDS == DF_K_NKINDS, "timing kinds follow the DF_K_* list");
 
 struct TScope {
@@ -297,7 +297,7 @@ void level_step(df_run *R, int l, const double *dtp, double scale, int rem, int 
   // keeps its role, so the launches of two consecutive steps repeat exactly
   LevBufs Bx = Bt;
   if (!kc || kicked) Bx.q[c][1] = B.etmp;
-  if (Gf) dfk::front_sums(st, G, P, B, *Gf, R->buf[l + 1], R->xi[l] == 2);
+  if (Gf) { TScope t(R, K_FRONT); dfk::front_sums(st, G, P, B, *Gf, R->buf[l + 1], R->xi[l] == 2); }
   // level 0: the x and y passes in one launch, q[c] -> q[1-c] (under a finer
   // level with flux matching on its frontier)
   const bool fused = R->fuse_xy && dfk::transport_xy_fits(G);
@@ -447,8 +447,11 @@ static_assert(offsetof(Scal, t) == MAXLEV * sizeof(double), "the step lengths an
 // one coarse step under the criterion: read the per-level limits back, choose
 // the schedule, upload the step lengths and the new time, advance, log the force
 int criterion_step(df_run *R) {
-  if (!R->sig_valid) post_reduce(R);
-  dfk::step_final(R->stream, R->geo, R->buf, R->nl, R->phys, R->scal, R->flog, 0, 2);
+  {
+    TScope t(R, K_DT);
+    if (!R->sig_valid) post_reduce(R);
+    dfk::step_final(R->stream, R->geo, R->buf, R->nl, R->phys, R->scal, R->flog, 0, 2);
+  }
   Scal h;
   int rc = hip_check(hipMemcpyAsync(&h, R->scal, sizeof(Scal), hipMemcpyDeviceToHost, R->stream), "limits copy");
   if (!rc) rc = hip_check(hipStreamSynchronize(R->stream), "limits copy");
@@ -462,8 +465,11 @@ int criterion_step(df_run *R) {
                  "step upload");
   if (rc) return rc;
   cycle(R, 0);
-  post_reduce(R);
-  dfk::step_final(R->stream, R->geo, R->buf, R->nl, R->phys, R->scal, R->flog, 1, 0);
+  {
+    TScope t(R, K_FORCE);
+    post_reduce(R);
+    dfk::step_final(R->stream, R->geo, R->buf, R->nl, R->phys, R->scal, R->flog, 1, 0);
+  }
   return launch_check("df_step");
 }
 
