@@ -329,7 +329,7 @@ void level_step(df_run *R, int l, const double *dtp, double scale, int rem, int 
   // written)
   Scal *post = R->nl == 1 ? R->scal : nullptr;
   bool zf = false;
-  if (R->fuse_zf && post && dfk::transport_z_finish_fits(G)) {
+  if (R->fuse_zf && kc && post && dfk::transport_z_finish_fits(G)) {
     TScope t(R, K_ZFINISH);
     zf = dfk::transport_z_finish(st, G, P, B, Bt.v, cy, dtp, scale, 0.5 * scale, post, R->segs);
   } else if (zff) {
