@@ -3600,17 +3600,27 @@ __device__ __forceinline__ void zfinish_body(Geo G, Phys P, MarchArgs<T> M, Kick
       o.y = fabs(a.y);
       return o;
     };
-    auto kickv = [&](V vf, V drm, V dem, V dcr, V der, V xr, V dm, V dr_) -> V {
+    // A rebuilt face velocity a / b before its kick.  On level 0 the quotient is
+    // rounded, then kicked, as k_kick0p's pairs are; a finer level's dividend
+    // and reciprocal go into the kick's multiply-add unrounded, as in k_kick: in
+    // FP32 the quotient's own rounding made the velocities of 4 x 128^3 2.5 %
+    // noisier (rms of vz over 40 steps 9.75e-11 against 9.50e-11).
+    struct Quot {
+      V a, r;
+    };
+    auto rebuild = [&](int d, V ppm, V pmc, V drm, V dcr) -> Quot {
+      const T vb = (T)vback(P, d);
+      const V a = ppm + pmc - vb * (drm + dcr), b = T(2) * rho0 + drm + dcr;
+      return L0 ? Quot{qdiv(a, b), V(1)} : Quot{a, qdiv(V(T(1)), b)};
+    };
+    auto kickv = [&](Quot f, V drm, V dem, V dcr, V der, V xr, V dm, V dr_) -> V {
       const V rface = rho0 + T(0.5) * (drm + dcr);
       const V gradp = qdiv(gm1 * (der - dem), dx * rface);
       const V xm = xr - dx;
       const V gradphi = qdiv(GM * (xr + xm), dm * dr_ * (dm + dr_));
-      vf = vf - h * (gradp + gradphi);
-      return L0 ? vf : vf - h2 * (gradp + gradphi);
-    };
-    auto rebuild = [&](int d, V ppm, V pmc, V drm, V dcr) -> V {
-      const T vb = (T)vback(P, d);
-      return qdiv(ppm + pmc - vb * (drm + dcr), T(2) * rho0 + drm + dcr);
+      if constexpr (L0) return f.a - h * (gradp + gradphi);
+      const V g = gradp + gradphi;
+      return fmav<V>(V(-h2), g, fmav<V>(f.a, f.r, -(h * g)));
     };
     // the faces normal to d at row j, plane k and (XB 3) their images: a face's
     // image lies as far beyond the plane, normal velocities change sign
@@ -3673,7 +3683,7 @@ __device__ __forceinline__ void zfinish_body(Geo G, Phys P, MarchArgs<T> M, Kick
             dem.x = dec.x;
             ppm.x = ppc.x;
           }
-          V vf = rebuild(0, ppm, ldv(buf, r, 2), drm, drc);
+          const Quot f0 = rebuild(0, ppm, ldv(buf, r, 2), drm, drc);
           V dmx;
           dmx.y = dcen.x;
           if (lx > 0) {
@@ -3684,7 +3694,7 @@ __device__ __forceinline__ void zfinish_body(Geo G, Phys P, MarchArgs<T> M, Kick
             xb.y = xb.x;
             dmx.x = qsqrtv(r2of(xb, yc, zcen)).x;
           }
-          vf = kickv(vf, drm, dem, drc, dec, xcx, dmx, dcen);
+          const V vf = kickv(f0, drm, dem, drc, dec, xcx, dmx, dcen);
           put_face(0, c, j, k, vf);
           if constexpr (L0) {
             const V a = vabs((T)vback(P, 0) + vf);
@@ -3703,11 +3713,11 @@ __device__ __forceinline__ void zfinish_body(Geo G, Phys P, MarchArgs<T> M, Kick
           const V pmy = ldv(buf, r, 4), ppy = ldv(buf, r, 5);
           const bool lo = j > y0;
           const V drm = lo ? ldv(buf, r - 1, 0) : drc, dem = lo ? ldv(buf, r - 1, 1) : dec;
-          V vf = rebuild(1, lo ? ldv(buf, r - 1, 5) : ppy, pmy, drm, drc);
+          const Quot f0 = rebuild(1, lo ? ldv(buf, r - 1, 5) : ppy, pmy, drm, drc);
           // the row below: its walkers' distances and sound speeds (the ghost
           // row's distance at y = 0)
           const V dmb = share && lo ? ldv(buf, r - 1, ZF_DIST) : qsqrtv(r2of(xcx, xcen<T>(G, 1, j - 1), zcen));
-          vf = kickv(vf, drm, dem, drc, dec, V(yc), dmb, dcen);
+          V vf = kickv(f0, drm, dem, drc, dec, V(yc), dmb, dcen);
           if (XB == 3 && !lo) vf = V(0);  // the mirror plane
           put_face(1, c, j, k, vf);
           if constexpr (L0) {
@@ -3718,8 +3728,7 @@ __device__ __forceinline__ void zfinish_body(Geo G, Phys P, MarchArgs<T> M, Kick
           if (L0 && j == G.n[1] - 1) {
             const T xr = xcen<T>(G, 1, j + 1);
             const V dr_ = qsqrtv(r2of(xcx, xr, zcen));
-            V vh = rebuild(1, ppy, pmy, drc, drc);
-            vh = kickv(vh, drc, dec, drc, dec, V(xr), dcen, dr_);
+            const V vh = kickv(rebuild(1, ppy, pmy, drc, drc), drc, dec, drc, dec, V(xr), dcen, dr_);
             gstv<V>(K.v[1], c + (idx_t)G.sy, vh);
             vmax(vabs(vh) + cs_own);
           }
@@ -3730,9 +3739,9 @@ __device__ __forceinline__ void zfinish_body(Geo G, Phys P, MarchArgs<T> M, Kick
           const V pmz = ldv(buf, r, 6);
           const bool lo = k > z0;
           const V drm = lo ? zb.r : drc, dem = lo ? zb.e : dec;
-          V vf = rebuild(2, lo ? zb.p : ppz, pmz, drm, drc);
+          const Quot f0 = rebuild(2, lo ? zb.p : ppz, pmz, drm, drc);
           const V dmb = lo ? zb.d : qsqrtv(r2of(xcx, yc, xcen<T>(G, 2, k - 1)));
-          vf = kickv(vf, drm, dem, drc, dec, V(zcen), dmb, dcen);
+          V vf = kickv(f0, drm, dem, drc, dec, V(zcen), dmb, dcen);
           if (XB == 3 && !lo) vf = V(0);
           put_face(2, c, j, k, vf);
           if constexpr (L0) {
@@ -3743,8 +3752,7 @@ __device__ __forceinline__ void zfinish_body(Geo G, Phys P, MarchArgs<T> M, Kick
           if (L0 && k == G.n[2] - 1) {
             const T xr = xcen<T>(G, 2, k + 1);
             const V dr_ = qsqrtv(r2of(xcx, yc, xr));
-            V vh = rebuild(2, ppz, pmz, drc, drc);
-            vh = kickv(vh, drc, dec, drc, dec, V(xr), dcen, dr_);
+            const V vh = kickv(rebuild(2, ppz, pmz, drc, drc), drc, dec, drc, dec, V(xr), dcen, dr_);
             gstv<V>(K.v[2], c + (idx_t)G.sz, vh);
             vmax(vabs(vh) + cs_own);
           }
