@@ -77,10 +77,10 @@ typedef struct df_run df_run;
  *               carries two sub-cycles without a refill, Sect. 3.2.1);
  *  seed, noise_amp : every active density is multiplied by 1 + noise_amp (2U-1),
  *               U uniform in [0,1) from a counter-based SplitMix64 stream;
- *  tile_chunk : cells per column segment of the streaming y and z transport
- *               passes (0: chosen per pass, 16 for FP32 storage and for
- *               FP64 32 on one level and 8 on nested meshes where these fill
- *               the GPU, shorter or longer ones where they do not; 2..256),
+ *  tile_chunk : cells per column segment of the y and z transport passes, fused
+ *               or apart (0: chosen per launch from the blocks it makes, so
+ *               that they fill the GPU in whole rounds; 2..256, of which the
+ *               finer levels' fused x + y pass takes at least 16),
  *               a launch-shape parameter that does not change results;
  *  nx1, ny1, nz1 : cells of every level >= 1 (0: those of level 0), each a
  *               multiple of 4, >= 16 and at most twice level 0's count.  Level

@@ -299,15 +299,16 @@ class Run:
         _ck(_load().df_set_boundaries(self._h, int(mode)))
 
     def set_transport_fusion(self, on: bool) -> None:
-        """fuse the x and y transport passes of level 0 and of the finer levels where they qualify (default on)"""
+        """the x and y transport passes of every level in one launch (default on)"""
         _ck(_load().df_set_transport_fusion(self._h, int(bool(on))))
 
     def set_kick_fusion(self, on: bool) -> None:
-        """kick and compress in one launch where it qualifies: level 0, and the finer levels in FP32 (default on)"""
+        """first kick and compression in one launch (default on); off while the viscosity is on"""
         _ck(_load().df_set_kick_fusion(self._h, int(bool(on))))
 
     def set_finish_fusion(self, on: bool) -> None:
-        """fuse a single-level step's z pass with the rebuild and kick where it qualifies (default on)"""
+        """z pass, velocity rebuild and second kick in one launch on a single level with the default boundaries and on
+        finer levels (default on)"""
         _ck(_load().df_set_finish_fusion(self._h, int(bool(on))))
 
     def set_step_graphs(self, on: bool) -> None:

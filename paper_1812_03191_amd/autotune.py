@@ -5,6 +5,8 @@ cells: short segments give more waves but reload more halo cells, long ones the
 reverse, and the best length depends on the mesh, the storage type and how
 full the GPU is.  The choice changes only the launch shape, never the results
 (each face transfer is computed the same way whichever segment holds it).
+The candidates are fixed lengths; 0, the library's own choice per launch, is
+what a run or job created without the tuner takes.
 ``best_chunk`` times each candidate and caches the winner per (mesh,
 precision, context) in a JSON file (``DFMESH_TUNE_CACHE`` or
 ``~/.cache/dfmesh/autotune.json``):

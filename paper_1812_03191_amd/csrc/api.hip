@@ -75,7 +75,7 @@ struct df_run {
   bool bound = false;
   bool ready = false;
   bool sig_valid = false;  // the signal-speed partials are those of the current state
-  bool fuse_xy = true;     // fuse the x and y passes where transport_xy applies
+  bool fuse_xy = true;     // fuse the x and y passes
   bool fuse_kc = true;     // fuse the first kick and the compression (viscosity off)
   bool fuse_zf = true;     // fuse the z pass with the rebuild, the kick and (single level) the end-of-step partials
   bool slot_mode = false;  // single level: the kicks take the step length from the signal-speed slots
@@ -298,17 +298,13 @@ void level_step(df_run *R, int l, const double *dtp, double scale, int rem, int 
   LevBufs Bx = Bt;
   if (!kc || kicked) Bx.q[c][1] = B.etmp;
   if (Gf) { TScope t(R, K_FRONT); dfk::front_sums(st, G, P, B, *Gf, R->buf[l + 1], R->xi[l] == 2); }
-  // level 0: the x and y passes in one launch, q[c] -> q[1-c] (under a finer
-  // level with flux matching on its frontier)
-  const bool fused = R->fuse_xy && dfk::transport_xy_fits(G);
-  // a finer level: its x and y passes in one launch too
-  const bool fused_fine = R->fuse_xy && !G.bc;
+  // the x and y passes in one launch, q[c] -> q[1-c], with flux matching on the
+  // level's frontiers
+  const bool fused = R->fuse_xy;
   if (fused) {
     TScope t(R, K_PASSXY);
-    dfk::transport_xy(st, G, P, Bx, c, dtp, scale, R->segs);
-  } else if (fused_fine) {
-    TScope t(R, K_PASSXY);
-    dfk::transport_xy_fine(st, Gy, P, Bx, c, dtp, scale, R->segs, sub);
+    if (G.bc) dfk::transport_xy(st, G, P, Bx, c, dtp, scale, R->segs);
+    else dfk::transport_xy_fine(st, Gy, P, Bx, c, dtp, scale, R->segs, sub);
   } else {
     // quadrant: a middle level takes the finer level's frontier transfers,
     // whose images lie beyond the planes: the transported set's images are
@@ -322,7 +318,7 @@ void level_step(df_run *R, int l, const double *dtp, double scale, int rem, int 
   }
   // the z pass and the rebuild take the set the y pass wrote (q[c] after
   // separate passes, q[1-c] after the fused ones)
-  const int cy = (fused || fused_fine) ? 1 - c : c;
+  const int cy = fused ? 1 - c : c;
   // a single-level step ends here: the same launch forms the force and the
   // next step's signal-speed partials; on level 0 without a finer level the z
   // pass joins them (only the new density, energy and face velocities are
@@ -642,9 +638,10 @@ int df_init_mesh(const df_mesh_desc *d, df_run **out) {
   R->desc = *d;
   R->nl = d->nlevels;
   R->esz = d->precision == DF_FP32 ? 4 : 8;
-  // the finer levels' one-column walks (FP64, 4 waves per SIMD) hide their
-  // latency with more, shorter segments: on 4 levels of 128^3, 8 cells run the
-  // coarse step 5 % faster than 32, which suits level 0's fused passes
+  // segments of the streaming y and z passes (and, beside other runs' launches,
+  // of the fused ones): the one-column walks of a nested FP64 run (4 waves per
+  // SIMD) hide their latency with more, shorter segments, 5 % of a coarse step
+  // of 4 levels of 128^3 between 8 cells and 32 when every level took them
   R->segs.cells = d->tile_chunk;
   R->segs.dflt = d->precision == DF_FP32 ? 16 : (d->nlevels > 1 ? 8 : 32);
   R->quad = d->quadrant == 1;

@@ -77,9 +77,12 @@ struct Scal {
 
 // Cells per segment of the walking launches (the streaming y and z passes, the
 // fused x + y passes, the fused z pass and step end), a launch shape that does
-// not change results.  cells > 0: that many.  cells = 0: dflt where the launch
-// then fills its share of the GPU, else shorter ones (seg_cells).  share: runs
-// whose launches run beside this one's (the engine's jobs).
+// not change results.  cells > 0: that many.  cells = 0: for a run alone the
+// fused passes take the length of least time over their blocks and rounds
+// (walk_cells); the streaming passes, and every pass beside other runs, take
+// dflt where the launch then fills its share of the GPU, else shorter ones
+// (seg_cells).  share: runs whose launches run beside this one's (the engine's
+// jobs).
 struct Segs {
   int cells = 0;
   int dflt = 16;
@@ -161,11 +164,9 @@ void transport_pass(hipStream_t st, int dir, const Geo &G, const Phys &P, LevBuf
                     const double *dtp, double fac, const Segs &segs,
                     int sub = 0);
 // fused x and y passes q[src] -> q[1-src] of level 0; under a finer level its
-// frontier takes the transfers of B.fsum.  false, launching nothing, when the
-// level does not qualify (a finer one)
-bool transport_xy(hipStream_t st, const Geo &G, const Phys &P, LevBufs &B, int src, const double *dtp,
+// frontier takes the transfers of B.fsum
+void transport_xy(hipStream_t st, const Geo &G, const Phys &P, LevBufs &B, int src, const double *dtp,
                   double fac, const Segs &segs);
-bool transport_xy_fits(const Geo &G);
 // fused x and y passes q[src] -> q[1-src] of a finer level (no boundary
 // conditions): G carries the y pass's margins; the entries written and the
 // frontier transfers taken and accumulated are those of the separate x and y

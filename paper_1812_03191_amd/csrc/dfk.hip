@@ -3376,9 +3376,8 @@ struct ZfLds {
 // A walker's sink: the plane's new departures into its row slot of the
 // current buffer, the density and energy of a band row (OUT) also to the
 // output set -- for the segment's own planes only: the plane below it
-// belongs to the segment below, whose block writes it (its value there may
-// differ in the last bit, its first face transfer being formed by the walk's
-// first step rather than its loop); done() hands the plane over.
+// belongs to the segment below, whose block writes it (the same value: see
+// march_column; one writer per plane); done() hands the plane over.
 // In FP64 the walkers also take a share of the finisher's work on their
 // plane (the finisher's work per plane is about twice a walker's, and every
 // plane ends in a barrier): the first group the cells' sound speeds (from the
@@ -4506,8 +4505,10 @@ static int walk_cells(const Segs &s, int ext, long cols, long fill, int rows) {
   }
   return best;
 }
-// Blocks of a fill, the best of 1/2 to 2 times as many over cubes of 24 to
-// 128 cells: the fused x + y pass two blocks per CU in FP64 and four in FP32,
+// Blocks of a fill, the best of 1/2 to 2 times as many over single-level cubes
+// of 24 to 128 cells, whose rows take one tile (the forms of longer rows and of
+// finer levels, whose registers allow other numbers of waves, take the same
+// figures): the fused x + y pass two blocks per CU in FP64 and four in FP32,
 // the fused z pass one and two, the streaming walks two; and the rows that the
 // fused passes' prologues take: for the z pass 5 to 12 do equally well, with 2
 // the finer levels of 128^3 (142 planes before their second sub-step) took
@@ -4646,8 +4647,6 @@ static void transport_pass_t(hipStream_t st, int dir, const Geo &G, const Phys &
     else march_launch<T, 1, 0, 1>(st, dir, G, P, M, gr, bl);
   }
 }
-bool transport_xy_fits(const Geo &G) { return G.bc != 0; }
-
 // tiles of a level-0 row of n cells: one while the row and, under bc 2, the
 // cell past it fit its lanes; else whole tiles as long as more cells are left
 // than the last one's, a part of a wave for the rest where it fits with the two
@@ -4665,10 +4664,9 @@ static XyTiles row_tiles(int n, int bc) {
 }
 
 template <typename T>
-static bool transport_xy_t(hipStream_t st, const Geo &G, const Phys &P, LevBufs &B, int src, const double *dtp,
+static void transport_xy_t(hipStream_t st, const Geo &G, const Phys &P, LevBufs &B, int src, const double *dtp,
                            double fac, const Segs &segs) {
   const int n = G.n[0];
-  if (!transport_xy_fits(G)) return false;
   PassArgs<T> A;
   A.b = active_box(G);
   for (int m = 0; m < NQ; ++m) {
@@ -4707,7 +4705,7 @@ static bool transport_xy_t(hipStream_t st, const Geo &G, const Phys &P, LevBufs 
   const dim3 gr((unsigned)(cols * nch)), bl(64, 4);
   const bool many = Bt.ntiles > 1 || Bt.parts;
   const int fr = A.fsum ? 1 : 0;
-  if (!fr && G.bc == 1 && !many && record(jk_xy<T>(n), XyJob<T>{G, P, A, M, Bt, gr.x})) return true;
+  if (!fr && G.bc == 1 && !many && record(jk_xy<T>(n), XyJob<T>{G, P, A, M, Bt, gr.x})) return;
   auto go = [&](auto w, auto xb) {
     constexpr int W = decltype(w)::value, XB = decltype(xb)::value;
     if (fr) DFK_LAUNCH((k_xyshared<T, W, XB, 1>), gr, bl, st, G, P, A, M, Bt);
@@ -4720,12 +4718,11 @@ static bool transport_xy_t(hipStream_t st, const Geo &G, const Phys &P, LevBufs 
   else if (one) go(c1, c1);
   else if (!many) go(c2, c1);
   else go(c2, std::integral_constant<int, 4>{});
-  return true;
 }
-bool transport_xy(hipStream_t st, const Geo &G, const Phys &P, LevBufs &B, int src, const double *dtp, double fac,
+void transport_xy(hipStream_t st, const Geo &G, const Phys &P, LevBufs &B, int src, const double *dtp, double fac,
                   const Segs &segs) {
-  if (P.fp32) return transport_xy_t<float>(st, G, P, B, src, dtp, fac, segs);
-  return transport_xy_t<double>(st, G, P, B, src, dtp, fac, segs);
+  if (P.fp32) transport_xy_t<float>(st, G, P, B, src, dtp, fac, segs);
+  else transport_xy_t<double>(st, G, P, B, src, dtp, fac, segs);
 }
 
 template <typename T>
