@@ -639,9 +639,9 @@ int df_init_mesh(const df_mesh_desc *d, df_run **out) {
   R->nl = d->nlevels;
   R->esz = d->precision == DF_FP32 ? 4 : 8;
   // segments of the streaming y and z passes (and, beside other runs' launches,
-  // of the fused ones): the one-column walks of a nested FP64 run (4 waves per
-  // SIMD) hide their latency with more, shorter segments, 5 % of a coarse step
-  // of 4 levels of 128^3 between 8 cells and 32 when every level took them
+  // of the fused ones): the one-column walks of a nested FP64 run hide their
+  // latency with more, shorter segments (8 cells against 32: 5 % of a coarse
+  // step of 4 levels of 128^3, measured when every finer level took these walks)
   R->segs.cells = d->tile_chunk;
   R->segs.dflt = d->precision == DF_FP32 ? 16 : (d->nlevels > 1 ? 8 : 32);
   R->quad = d->quadrant == 1;
