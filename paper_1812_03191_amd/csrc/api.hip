@@ -1660,9 +1660,11 @@ int df_engine_stats(df_engine *E, int64_t out[3]) {
 
 int df_engine_destroy(df_engine *E) {
   if (!E) return fail(DF_EINVAL, "null engine");
-  // a failed synchronisation is reported; the teardown below goes on (its
+  // the replays in flight read the graph's arguments and the job tables (main
+  // may be the null stream; without an admission stream nothing was launched).
+  // A failed synchronisation is reported; the teardown below goes on (its
   // destroy calls have nothing further to report)
-  const int rc = E->main ? hip_check(hipStreamSynchronize(E->main), "engine destroy") : DF_OK;
+  const int rc = E->admin ? hip_check(hipStreamSynchronize(E->main), "engine destroy") : DF_OK;
   engine_reap(E, true);
   if (E->exec) (void)hipGraphExecDestroy(E->exec);
   for (auto &t : E->tabs)
