@@ -43,6 +43,14 @@ int hip_check(hipError_t e, const char *where) {
 
 int launch_check(const char *where) { return hip_check(hipGetLastError(), where); }
 
+// Launches recorded into a capture: one that the runtime refuses leaves nothing
+// in the graph and no error at its end.  check() reports it, unless an error
+// was pending before the first of them.
+struct CaptureWatch {
+  const bool clean = hipPeekAtLastError() == hipSuccess;
+  int check(const char *where) const { return clean ? launch_check(where) : DF_OK; }
+};
+
 constexpr size_t ALIGN = 256;
 inline size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
@@ -563,10 +571,13 @@ int graph_steps(df_run *R, int k) {
     std::copy(R->cur, R->cur + R->nl, cur0);
     hipStream_t user = R->stream;
     R->stream = R->gstream;
+    const CaptureWatch watch;
     enqueue_steps(R, 2);
     R->stream = user;
+    const int missing = watch.check("graph capture launches");
     hipGraph_t g = nullptr;
     rc = hip_check(hipStreamEndCapture(R->gstream, &g), "graph capture end");
+    if (!rc) rc = missing;
     if (!rc) {
       rc = hip_check(hipGraphInstantiate(&R->gexec[s], g, nullptr, nullptr, 0), "graph instantiate");
       if (rc) R->gexec[s] = nullptr;
@@ -1388,6 +1399,7 @@ int engine_capture(df_engine *E) {
   // launches that run at once: one per worker stream with a job, and the batched ones
   const int nown = (int)std::min(act.size() - (size_t)E->batched, E->workers.size()) + (E->batched ? 1 : 0);
   size_t nw = 0;
+  const CaptureWatch watch;
   for (size_t q = 0; q < act.size(); ++q) {
     if (bat[q]) continue;
     EngineJob &J = E->jobs[act[q]];
@@ -1406,6 +1418,7 @@ int engine_capture(df_engine *E) {
     dfk::launch_jobs(E->cap, g.kind, base + g.off_e, reinterpret_cast<const unsigned *>(base + g.off_s), g.n,
                      g.nblocks);
   }
+  const int missing = watch.check("graph capture launches");
   for (size_t w = 0; !rc && w < E->workers.size(); ++w) {
     rc = hip_check(hipEventRecord(E->join[w], E->workers[w]), "graph join");
     if (!rc) rc = hip_check(hipStreamWaitEvent(E->cap, E->join[w], 0), "graph join");
@@ -1414,6 +1427,10 @@ int engine_capture(df_engine *E) {
   hipGraph_t g = nullptr;
   rc = hip_check(hipStreamEndCapture(E->cap, &g), "graph capture end");
   if (rc) return restore(rc);
+  if (missing) {
+    (void)hipGraphDestroy(g);
+    return restore(missing);
+  }
   rc = hip_check(hipGraphInstantiate(&E->exec, g, nullptr, nullptr, 0), "graph instantiate");
   (void)hipGraphDestroy(g);  // the instantiated graph does not need it
   if (rc) {
